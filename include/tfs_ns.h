@@ -69,15 +69,16 @@ int64_t tfs_ns_spectral_size(tfs_ns ns);
 /*
  * 1 when the solver transforms whole fields in batched hipFFT plans, 0 when it transforms
  * one plane at a time (hipFFT refuses the batched layout, planes `stride` apart, for some
- * sizes; the results are the same).
+ * sizes, and it is not used with an odd stride and an even last axis, which hipFFT gets wrong;
+ * the results are the same).
  */
 int tfs_ns_batched(tfs_ns ns);
 
 /*
  * Choose the transform form: on = 0 transforms one plane at a time, on = 1 asks for the
  * batched plans (the form tfs_ns_create tries first).  Synchronises the device and remakes
- * the plans.  Errors: TFS_EINVAL (null solver), TFS_EUNSUPPORTED (on = 1 and hipFFT
- * refuses the batched layout; the solver then transforms one plane at a time), TFS_EHIP.
+ * the plans.  Errors: TFS_EINVAL (null solver), TFS_EUNSUPPORTED (on = 1 and the
+ * batched layout cannot be had; the solver then transforms one plane at a time), TFS_EHIP.
  */
 tfs_status tfs_ns_set_batched(tfs_ns ns, int on);
 

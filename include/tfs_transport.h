@@ -62,7 +62,8 @@ tfs_status tfs_transport_destroy(tfs_transport tr);
  * time (batched hipFFT plans, tried at creation; 2-D grids of 160000 points or more with axes of
  * at most 1024 points and no prime factor above 5 use kernels of the library's own), 0 when planes
  * go through hipFFT one at a time; set_batched(0) forces planes one at a time, set_batched(1) asks
- * for whole fields (TFS_EUNSUPPORTED if hipFFT refuses the layout).  Results agree to rounding.
+ * for whole fields (TFS_EUNSUPPORTED if hipFFT refuses the layout, or gets it wrong: an odd stride with
+ * an even last axis).  Results agree to rounding.
  */
 int tfs_transport_batched(tfs_transport tr);
 tfs_status tfs_transport_set_batched(tfs_transport tr, int on);

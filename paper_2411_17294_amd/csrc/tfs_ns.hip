@@ -283,6 +283,7 @@ hipfftResult make_plan(tfs_ns_s* s, hipfftHandle* h, bool forward, int batch) {
 tfs_status make_plans(tfs_ns_s* s, bool try_batched) {
   const int d = s->dim, c = d * (d + 1) / 2;
   const int batch[4] = {d, c, d, d * d};
+  if (!tfs::batch_distance_ok(s->n[d - 1], s->stride)) try_batched = false;
   hipfftResult r = HIPFFT_SUCCESS;
   for (int i = 0; i < 4 && r == HIPFFT_SUCCESS && try_batched; ++i) {
     r = make_plan(s, &s->plan[i], i < 2, batch[i]);

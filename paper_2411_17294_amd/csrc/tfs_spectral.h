@@ -31,4 +31,9 @@ __device__ __forceinline__ void wave_numbers(const SpecGeom& g, int64_t q, int64
 __host__ __device__ inline double axis_k0(const SpecGeom& g, int j) { return j == 0 ? g.k0 : (j == 1 ? g.k1 : g.k2); }
 __host__ __device__ inline int64_t axis_n(const SpecGeom& g, int j) { return j == 0 ? g.n0 : (j == 1 ? g.n1 : g.n2); }
 
+// Whether a batched hipFFT plan may take real planes `dist` values apart.  Real lines of even length
+// are transformed as half as many complex values, so the plane distance counts in pairs: with an odd
+// one every plane but the first came out wrong, without an error.
+inline bool batch_distance_ok(int64_t last_axis, int64_t dist) { return last_axis % 2 != 0 || dist % 2 == 0; }
+
 }  // namespace tfs
