@@ -94,3 +94,19 @@ def test_transport_step_reports_every_failed_call(fake, shape, method):
     code = "\n".join(f"steps({shape}, {whole}, {method}, {tol}, {scheme})"
                      for whole in (True, False) for tol in (0.0, 1e-9) for scheme in (0, 1))
     child(fake, code)
+
+
+def test_line_kernels_keep_no_batched_plans(fake):
+    """A transport object holds the two single-plane plans, and the four batched ones only where it uses
+    them."""
+    child(fake, """
+for shape, n in (((400, 405), 2), ((12, 16), 6), ((8, 6, 10), 6)):
+    tr = transport(shape, math.prod(shape), 3)
+    assert F.fake_plans() == n and L.tfs_transport_batched(tr) == 1, (shape, F.fake_plans())
+    tfs.check(L.tfs_transport_set_batched(tr, 0))
+    assert F.fake_plans() == 2 and L.tfs_transport_batched(tr) == 0, (shape, F.fake_plans())
+    tfs.check(L.tfs_transport_set_batched(tr, 1))
+    assert F.fake_plans() == n and L.tfs_transport_batched(tr) == 1, (shape, F.fake_plans())
+    tfs.check(L.tfs_transport_destroy(tr))
+    assert F.fake_plans() == 0
+""")
