@@ -110,3 +110,15 @@ for shape, n in (((400, 405), 2), ((12, 16), 6), ((8, 6, 10), 6)):
     tfs.check(L.tfs_transport_destroy(tr))
     assert F.fake_plans() == 0
 """)
+
+
+def test_no_host_memory_for_the_line_kernels(fake):
+    """No exception leaves the C entry: without memory for the tables the object uses the library's
+    transforms."""
+    child(fake, """
+F.fake_refuse_new(4096)
+tr = transport((400, 405), 162000, 3)
+F.fake_refuse_new(0)
+assert F.fake_plans() == 6 and L.tfs_transport_batched(tr) == 1
+tfs.check(L.tfs_transport_destroy(tr))
+""")
