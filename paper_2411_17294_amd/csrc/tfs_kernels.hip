@@ -652,7 +652,7 @@ struct ExpArgs {
   const KT* kb;         // kappa_b or null
   const double* Xn;     // X^n     [c][stride]
   double* Xo;           // X^{n+1} [c][stride]
-  const MT* Yn;         // Y^n (m * c * stride elements, tiled); at n = 0 any readable level (not used)
+  const MT* Yn;         // Y^n (m * c * stride elements, tiled); not read at n = 0
   MT* Yo;               // Y^{n+1} (may be Yn: each lane reads a mode before writing it)
   double* tau;          // [c][stride] or null
   double* Hout;         // SPLIT: H [c][stride]
@@ -684,21 +684,24 @@ __device__ __forceinline__ void exp_stream(const ExpArgs<MT, KT>& a, const WaveA
   double pack[kPack];
   load_pack(a.coef, m, 0, pack);
   struct Buf { MT y[V]; };
-  stream_modes<A, Buf>(
-      m, [&](int k, Buf& b) { load_v<true, MT, V, true>(at(yn0 + k * kT, opaque(w.om)), V, b.y); },
-      [&](int k, const Buf& b) {
-        const double ek = pack[kPackE], fk = pack[kPackF], lk = pack[kPackLdt], ok = pack[kPackOneME], qk = pack[kPackQ];
-        load_pack(a.coef, m, k + 1 < m ? k + 1 : k, pack);
-        MT out[V];
+  auto use = [&](int k, const Buf& b) {
+    const double ek = pack[kPackE], fk = pack[kPackF], lk = pack[kPackLdt], ok = pack[kPackOneME], qk = pack[kPackQ];
+    load_pack(a.coef, m, k + 1 < m ? k + 1 : k, pack);
+    MT out[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          const double y = first ? -qk * Xc[v] : (double)b.y[v];
-          out[v] = (MT)(ek * y + fk * Xc[v]);
-          H[v] += ok * y;
-          two_sum_acc(Gs[v], Ge[v], mul_rn(lk, (double)out[v]));
-        }
-        store_v<true, MT, V, true>(at(yo0 + k * kT, opaque(w.om)), V, out);
-      });
+    for (int v = 0; v < V; ++v) {
+      const double y = first ? -qk * Xc[v] : (double)b.y[v];
+      out[v] = (MT)(ek * y + fk * Xc[v]);
+      H[v] += ok * y;
+      two_sum_acc(Gs[v], Ge[v], mul_rn(lk, (double)out[v]));
+    }
+    store_v<true, MT, V, true>(at(yo0 + k * kT, opaque(w.om)), V, out);
+  };
+  if (first) {   // level 0's modes are -q_k X^0: nothing to read
+    for (int k = 0; k < m; ++k) use(k, Buf{});
+  } else {
+    stream_modes<A, Buf>(m, [&](int k, Buf& b) { load_v<true, MT, V, true>(at(yn0 + k * kT, opaque(w.om)), V, b.y); }, use);
+  }
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     shX[v] = Xc[v];
@@ -1116,7 +1119,7 @@ hipError_t exp_dispatch(const tfs_plan_s* p, int64_t n, const void* ka, const vo
   a.kb = (n >= 1) ? static_cast<const KT*>(kb) : nullptr;
   a.Xn = L.Xn;
   a.Xo = L.Xo;
-  a.Yn = static_cast<const MT*>(n == 0 ? L.Yo : L.Yn);   // no branch in the stream: level 0's values are not used
+  a.Yn = static_cast<const MT*>(L.Yn);
   a.Yo = static_cast<MT*>(L.Yo);
   a.tau = tau;
   a.Hout = nullptr;
@@ -1167,7 +1170,7 @@ hipError_t exp_split_dispatch(const tfs_plan_s* p, int64_t n, const double* ka, 
   a.kb = (n >= 1) ? kb : nullptr;
   a.Xn = L.Xn;
   a.Xo = L.Xo;
-  a.Yn = static_cast<const MT*>(n == 0 ? L.Yo : L.Yn);   // no branch in the stream: level 0's values are not used
+  a.Yn = static_cast<const MT*>(L.Yn);
   a.Yo = static_cast<MT*>(L.Yo);
   a.tau = G;
   a.Hout = H;
