@@ -1021,15 +1021,21 @@ __device__ __forceinline__ void start_adj_group(const StartAdjArgs<MT, KT>& a, i
     const double vk = load_uniform(a.coef + kRowV * m + k);
     const double bk = a.zform ? load_uniform(a.coef + kRowBeta * m + k) : 0.0;
     double ac = 0.0, au = 0.0, av = 0.0;
+    // all of a mode's loads before its arithmetic: left to the scheduler, some instances wait for one
+    // after the other (3-D, FP32 modes, m = 32, 500000 points: 637 us, with the barrier 364)
+    MT h1[C][V], h2[C][V];
 #pragma unroll
     for (int s = 0; s < C; ++s) {
-      MT h1[V], h2[V];
-      load_v<true, MT, V, true>(h1p + ((int64_t)k * C + s) * T, V, h1);
-      load_v<true, MT, V, true>(h2p + ((int64_t)k * C + s) * T, V, h2);
+      load_v<true, MT, V, true>(h1p + ((int64_t)k * C + s) * T, V, h1[s]);
+      load_v<true, MT, V, true>(h2p + ((int64_t)k * C + s) * T, V, h2[s]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < C; ++s) {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const double y0 = -0.5 * (double)h1[v];
-        const double y1 = 2.0 * (double)h1[v] - 0.5 * (double)h2[v];
+        const double y0 = -0.5 * (double)h1[s][v];
+        const double y1 = 2.0 * (double)h1[s][v] - 0.5 * (double)h2[s][v];
         X0b[s][v] += -ck * y0 - bk * y1;
         X1b[s][v] += uk * y1;
         X2b[s][v] += vk * y1;

@@ -35,3 +35,19 @@ def test_first_exponential_step_reads_no_modes():
     t = [best_us(lambda: p.step(n, k, k, X, Y, tau)) for n in (0, 3)]
     print(f"exponential step: n=0 {t[0]:.1f} us, n=3 {t[1]:.1f} us", flush=True)
     assert t[0] < 0.75 * t[1]
+
+
+def test_start_adjoint_is_not_slower_with_fp64_gradients():
+    """FP64 velocity gradients add 36 bytes a point to 1500 of modes."""
+    P, m = 500000, 32
+    w, lam, _ = osoe.soe_fit(0.5, m, 1e-3, 1.0)
+    t = []
+    for kappa in ("fp32", "fp64"):
+        p = tfs.Plan(3, P, w, lam, 0.5, 1.0, 0.1, 1e-3, 8, precision="fp32_modes", kappa=kappa)
+        X, Y, tau, _ = p.alloc()
+        ka, Xb, Hb = p.kappa_tensor(), torch.zeros_like(X), torch.zeros_like(Y)
+        kb = torch.zeros((9, p.stride), dtype=torch.float64, device="cuda")
+        pb = torch.zeros(p.pbar_size, dtype=torch.float64, device="cuda")
+        t.append(best_us(lambda: p.step_adjoint(0, ka, None, X[0], None, X[1], Y, Y, Xb, Hb, pb, taubar=tau, kappabar_a=kb)))
+    print(f"start adjoint: FP32 gradients {t[0]:.1f} us, FP64 {t[1]:.1f} us", flush=True)
+    assert t[1] < 1.3 * t[0]
