@@ -500,10 +500,11 @@ int64_t tfs_plan_tile(tfs_plan plan);
 
 /*
  * Launch tuning; does not change results beyond rounding-order-free choices:
- *   "vec"          points per lane of the forward step: 0 = the width up to 2 (4 for TFS_SCHEME_EXP
- *                  with TFS_FP32_MODES) that the alignment of the fields allows and that fills the
- *                  device best (default), or 1, 2 (and 4 for TFS_FP32_MODES); a width the alignment
- *                  does not allow falls back to 1 at launch.
+ *   "vec"          points per lane of the forward steps and the start-up: 0 (default) = 2 (4 for
+ *                  TFS_SCHEME_EXP with TFS_FP32_MODES), or 1, 2 (and 4 for TFS_FP32_MODES).  Where the
+ *                  alignment of the fields does not allow a lane's points in one access, a step of
+ *                  whole blocks takes 2 (FP64) or 4 (FP32 modes) with an access each, and every other
+ *                  launch, or any with "vec" = 1, one point.
  *   "adj_vec"      points per lane of the BDF2 adjoint: 0 (default: 2 for FP32 modes, 1 for FP64), 1 or 2.
  *   "grid_per_cu"  cap on blocks per compute unit of the grid-stride launches,
  *                  1..64 (default: 1 for TFS_FP64 plans, 16 for TFS_FP32_MODES plans; the forward

@@ -222,6 +222,29 @@ __device__ __forceinline__ WaveAddr wave_addr(int64_t pw, int lane, int64_t T, i
   return w;
 }
 
+// The points of a lane that holds V of a wave's 64 V: V consecutive ones (one wide access a plane), or,
+// APART, one of each 64 consecutive points (V accesses a plane, which need no alignment: a wave still
+// takes 64 V consecutive values of a plane in one go).
+template <int V, bool APART>
+struct LaneAddr {
+  WaveAddr w;
+  uint32_t om[APART ? V : 1];          // APART: the mode offset of each point
+  static constexpr int kStep = APART ? 64 : 1;   // points between a lane's points
+  static constexpr int kLane = APART ? 1 : V;    // points between neighbouring lanes' first points
+};
+
+template <typename MT, int C, int V, bool APART>
+__device__ __forceinline__ LaneAddr<V, APART> lane_addr(int64_t pw, int lane, int64_t T, int m) {
+  LaneAddr<V, APART> l;
+  l.w = wave_addr<MT, C, APART ? 1 : V>(pw, lane, T, m);
+  l.om[0] = l.w.om;
+  if constexpr (APART) {
+#pragma unroll
+    for (int v = 1; v < V; ++v) l.om[v] = wave_addr<MT, C, 1>(pw, lane + 64 * v, T, m).om;
+  }
+  return l;
+}
+
 // ------------------------------------------------------------------ vector memory access
 template <typename T, int V> struct VecOf { using type = T __attribute__((ext_vector_type(V))); };
 template <typename T> struct VecOf<T, 1> { using type = T; };
@@ -264,6 +287,37 @@ __device__ __forceinline__ void store_v(T* p, int nv, const T (&x)[V]) {
 #pragma unroll
     for (int i = 0; i < V; ++i)
       if (i < nv) p[i] = x[i];
+  }
+}
+
+// A lane's points of an FP64 plane (base: the wave's first point).
+template <int V, bool APART>
+__device__ __forceinline__ void load_points(const double* base, const LaneAddr<V, APART>& l, double (&o)[V]) {
+  if constexpr (APART) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) o[v] = *at(base + v * l.kStep, l.w.ox);
+  } else {
+    load_v<true, double, V>(at(base, l.w.ox), V, o);
+  }
+}
+
+// A lane's points of a mode plane, streamed (base: the wave's first point).
+template <typename MT, int V, bool APART>
+__device__ __forceinline__ void load_modes(const MT* base, const LaneAddr<V, APART>& l, MT (&o)[V]) {
+  if constexpr (APART) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) o[v] = __builtin_nontemporal_load(at(base, opaque(l.om[v])));
+  } else {
+    load_v<true, MT, V, true>(at(base, opaque(l.om[0])), V, o);
+  }
+}
+template <typename MT, int V, bool APART>
+__device__ __forceinline__ void store_modes(MT* base, const LaneAddr<V, APART>& l, const MT (&x)[V]) {
+  if constexpr (APART) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) __builtin_nontemporal_store(x[v], at(base, opaque(l.om[v])));
+  } else {
+    store_v<true, MT, V, true>(at(base, opaque(l.om[0])), V, x);
   }
 }
 

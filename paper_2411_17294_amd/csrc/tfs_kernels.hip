@@ -175,19 +175,20 @@ __device__ __forceinline__ void load_pack(const double* coef, int m, int k, doub
 // ZF: the shifted mode form Z_k^j = Y_k^j - beta_k X^{j-1}: the history is read back as
 // h^_k = 2 Z_k^n - Z_k^{n-1}/2 + beta_k B with B = 2 X^{n-1} - X^{n-2}/2, and the new level is
 // stored as Z_k^{n+1} = d_k h^_k + d_k c_k P - beta_k X^n (still independent of X^{n+1}).
-template <int D, typename MT, typename KT, int V, bool ZF, int A>
-__device__ __forceinline__ void bdf2_stream(const Bdf2Args<MT, KT>& a, const WaveAddr& w, int s, double* shP,
+template <int D, typename MT, typename KT, int V, bool APART, bool ZF, int A>
+__device__ __forceinline__ void bdf2_stream(const Bdf2Args<MT, KT>& a, const LaneAddr<V, APART>& l, int s, double* shP,
                                             double* shG) {
+  const WaveAddr& w = l.w;
   const int64_t st = a.stride, T = a.tile;
   const int m = a.m;
   // P = 2 X^n - X^{n-1}/2 (and B = 2 X^{n-1} - X^{n-2}/2 in the shifted form)
   double xn[V], xm[V], P[V], B[V], Gs[V], Ge[V];
-  load_v<true, double, V>(at(a.Xn + s * st + w.pw, w.ox), V, xn);
-  load_v<true, double, V>(at(a.Xm + s * st + w.pw, w.ox), V, xm);
+  load_points(a.Xn + s * st + w.pw, l, xn);
+  load_points(a.Xm + s * st + w.pw, l, xm);
   if constexpr (ZF) {
     double xmm[V];
     if (a.Xmm) {
-      load_v<true, double, V>(at(a.Xmm + s * st + w.pw, w.ox), V, xmm);
+      load_points(a.Xmm + s * st + w.pw, l, xmm);
     } else {
 #pragma unroll
       for (int v = 0; v < V; ++v) xmm[v] = 0.0;
@@ -211,9 +212,8 @@ __device__ __forceinline__ void bdf2_stream(const Bdf2Args<MT, KT>& a, const Wav
   stream_modes<A, Buf>(
       m,
       [&](int k, Buf& b) {
-        const uint32_t om = opaque(w.om);
-        load_v<true, MT, V, true>(at(yn0 + k * kT, om), V, b.n);
-        load_v<true, MT, V, true>(at(ym0 + k * kT, om), V, b.m);
+        load_modes(yn0 + k * kT, l, b.n);
+        load_modes(ym0 + k * kT, l, b.m);
       },
       [&](int k, const Buf& b) {
         const double dk = pack[kPackD], dck = pack[kPackDC], ek = pack[kPackEta], bk = pack[kPackBeta];
@@ -230,12 +230,12 @@ __device__ __forceinline__ void bdf2_stream(const Bdf2Args<MT, KT>& a, const Wav
           }
           two_sum_acc(Gs[v], Ge[v], mul_rn(ek, h));
         }
-        store_v<true, MT, V, true>(at(yo0 + k * kT, opaque(w.om)), V, out);
+        store_modes(yo0 + k * kT, l, out);
       });
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    shP[v] = P[v];
-    shG[v] = Gs[v] + Ge[v];
+    shP[v * l.kStep] = P[v];
+    shG[v * l.kStep] = Gs[v] + Ge[v];
   }
 }
 
@@ -321,7 +321,7 @@ __device__ __forceinline__ void bdf2_point(const Bdf2Args<MT, KT>& a, int64_t pw
 // SPLIT: the step without its local solve, for a caller that solves a spatially coupled
 // system for X^{n+1}: the modes advance as usual (in the Y-form they do not depend on
 // X^{n+1}), the point's right-hand side R goes to Xo and the history combination G to tau.
-template <int D, typename MT, typename KT, int V, bool DIAG, bool SP, bool SPLIT = false, bool ZF = false>
+template <int D, typename MT, typename KT, int V, bool APART, bool DIAG, bool SP, bool SPLIT = false, bool ZF = false>
 __global__ __launch_bounds__(SplitShape<D>::kThreads) void bdf2_kernel(const Bdf2Args<MT, KT> a) {
   constexpr int C = Sym<D>::C;
   __shared__ double sh[2][2 * C * SplitShape<D>::kGroups * 64 * V];
@@ -337,9 +337,11 @@ __global__ __launch_bounds__(SplitShape<D>::kThreads) void bdf2_kernel(const Bdf
     }
     double* shP = sh[half];
     double* shG = shP + C * NP;
-    const int p1 = sw.group * 64 * W, o = sw.s * NP + p1 + sw.lane * W;
-    if (p1 + sw.lane * W < left)
-      bdf2_stream<D, MT, KT, W, ZF, A>(a, wave_addr<MT, C, W>(pw + p1, sw.lane, a.tile, a.m), sw.s, shP + o, shG + o);
+    using L = LaneAddr<W, APART && W != 1>;
+    const int p1 = sw.group * 64 * W, o = sw.s * NP + p1 + sw.lane * L::kLane;
+    if (p1 + sw.lane * L::kLane < left)
+      bdf2_stream<D, MT, KT, W, APART && W != 1, ZF, A>(
+          a, lane_addr<MT, C, W, APART && W != 1>(pw + p1, sw.lane, a.tile, a.m), sw.s, shP + o, shG + o);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -668,14 +670,15 @@ struct ExpArgs {
 
 // The mode stream of component s at a wave's 64 groups of V points; H enters the solve only
 // (plain FP64 sum), G is the stress's near-cancelling term (compensated).
-template <int D, typename MT, typename KT, int V, int A>
-__device__ __forceinline__ void exp_stream(const ExpArgs<MT, KT>& a, const WaveAddr& w, int s, double* shX,
+template <int D, typename MT, typename KT, int V, bool APART, int A>
+__device__ __forceinline__ void exp_stream(const ExpArgs<MT, KT>& a, const LaneAddr<V, APART>& l, int s, double* shX,
                                            double* shH, double* shG) {
+  const WaveAddr& w = l.w;
   const int64_t T = a.tile;
   const int m = a.m;
   const bool first = a.s.first != 0;
   double Xc[V], H[V], Gs[V], Ge[V];
-  load_v<true, double, V>(at(a.Xn + s * a.stride + w.pw, w.ox), V, Xc);
+  load_points(a.Xn + s * a.stride + w.pw, l, Xc);
 #pragma unroll
   for (int v = 0; v < V; ++v) { H[v] = 0.0; Gs[v] = 0.0; Ge[v] = 0.0; }
   const MT* yn0 = a.Yn + w.tw + s * T;
@@ -695,18 +698,18 @@ __device__ __forceinline__ void exp_stream(const ExpArgs<MT, KT>& a, const WaveA
       H[v] += ok * y;
       two_sum_acc(Gs[v], Ge[v], mul_rn(lk, (double)out[v]));
     }
-    store_v<true, MT, V, true>(at(yo0 + k * kT, opaque(w.om)), V, out);
+    store_modes(yo0 + k * kT, l, out);
   };
   if (first) {   // level 0's modes are -q_k X^0: nothing to read
     for (int k = 0; k < m; ++k) use(k, Buf{});
   } else {
-    stream_modes<A, Buf>(m, [&](int k, Buf& b) { load_v<true, MT, V, true>(at(yn0 + k * kT, opaque(w.om)), V, b.y); }, use);
+    stream_modes<A, Buf>(m, [&](int k, Buf& b) { load_modes(yn0 + k * kT, l, b.y); }, use);
   }
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    shX[v] = Xc[v];
-    shH[v] = H[v];
-    shG[v] = Gs[v] + Ge[v];
+    shX[v * l.kStep] = Xc[v];
+    shH[v * l.kStep] = H[v];
+    shG[v * l.kStep] = Gs[v] + Ge[v];
   }
 }
 
@@ -768,7 +771,7 @@ __device__ __forceinline__ void exp_point(const ExpArgs<MT, KT>& a, int64_t pw, 
 // SPLIT: the step without its local solve, for a caller that solves a spatially coupled
 // system: X^{n+1} receives each point's right-hand side R, tau the compensated G and Hout the
 // H of the local system (the modes are written as usual: they do not depend on X^{n+1}).
-template <int D, typename MT, typename KT, int V, bool DIAG, bool SP, bool SPLIT = false>
+template <int D, typename MT, typename KT, int V, bool APART, bool DIAG, bool SP, bool SPLIT = false>
 __global__ __launch_bounds__(SplitShape<D>::kThreads) void exp_kernel(const ExpArgs<MT, KT> a) {
   constexpr int C = Sym<D>::C;
   __shared__ double sh[2][3 * C * SplitShape<D>::kGroups * 64 * V];
@@ -785,10 +788,11 @@ __global__ __launch_bounds__(SplitShape<D>::kThreads) void exp_kernel(const ExpA
     double* shX = sh[half];
     double* shH = shX + C * NP;
     double* shG = shH + C * NP;
-    const int p1 = sw.group * 64 * W, o = sw.s * NP + p1 + sw.lane * W;
-    if (p1 + sw.lane * W < left)
-      exp_stream<D, MT, KT, W, A>(a, wave_addr<MT, C, W>(pw + p1, sw.lane, a.tile, a.m), sw.s, shX + o, shH + o,
-                                  shG + o);
+    using L = LaneAddr<W, APART && W != 1>;
+    const int p1 = sw.group * 64 * W, o = sw.s * NP + p1 + sw.lane * L::kLane;
+    if (p1 + sw.lane * L::kLane < left)
+      exp_stream<D, MT, KT, W, APART && W != 1, A>(
+          a, lane_addr<MT, C, W, APART && W != 1>(pw + p1, sw.lane, a.tile, a.m), sw.s, shX + o, shH + o, shG + o);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -834,7 +838,7 @@ int grid_for(const tfs_plan_s* p, int64_t ngroups) {
 
 bool aligned(const void* ptr, size_t bytes) { return ptr == nullptr || ((uintptr_t)ptr % bytes) == 0; }
 
-// Points per lane: the requested width, else the widest up to `widest` for which every plane start
+// Points per lane and access: the requested width, else the widest up to `widest` for which every plane start
 // and every group start is aligned to the vector size of each field (modes: V * sizeof(MT); the
 // other fields, FP64: V * 8).  widest: a lane loads 16 bytes of a mode or more (FP64: 2 points;
 // FP32: 2 points of BDF2's two levels, 4 of the exponential scheme's one); wider lanes only hold
@@ -876,6 +880,20 @@ double fill(const tfs_plan_s* p, int64_t per) {
   return rounds / std::ceil(rounds);
 }
 
+// Where the alignment allows no wide access a step of whole blocks still takes several points a lane,
+// each with its own access (LaneAddr, APART): a wave visits 1 KB of a mode plane at a time.  With one
+// point a lane it visits 256 bytes, which start and end within cache lines that other blocks share
+// (odd stride, m = 32, 262145 points, 3-D: FP32 exponential 152 us against 100, FP32 BDF2 199 against
+// 140, FP64 BDF2 286 against 260).  A grid of narrow rounds only keeps the smaller kernel (20001 points,
+// 3-D, FP32 BDF2: 19 us against 24).
+template <typename MT>
+constexpr int kApart = sizeof(MT) == 4 ? 4 : 2;
+
+template <typename MT>
+bool points_apart(const tfs_plan_s* p) {
+  return p->vec_override != 1 && split_grid(p, kApart<MT>).main > 0;
+}
+
 // Whether a step takes bdf2_wide_kernel: 2-D FP64 plans without a shifted form, two points a lane,
 // and enough points for two rounds of its blocks of 512 with the last round nearly full (262144
 // points, m = 32: 103 us against 108; 200001: 110 against 87, one round and a half).
@@ -892,42 +910,42 @@ int wide_blocks(const tfs_plan_s* p) {
   return (int)(g < cap ? g : cap);
 }
 
-template <int D, typename MT, typename KT, int V, bool DIAG, bool SP, bool ZF>
+template <int D, typename MT, typename KT, int V, bool APART, bool DIAG, bool SP, bool ZF>
 hipError_t bdf2_go_(const tfs_plan_s* p, Bdf2Args<MT, KT> a, double* diag_out) {
   const SplitGrid sg = split_grid(p, V);
   int grid = sg.grid;
   a.main = sg.main;
   a.wide = sg.wide;
   bool wide = false;
-  if constexpr (D == 2 && sizeof(MT) == 8 && !ZF) {
+  if constexpr (D == 2 && sizeof(MT) == 8 && !ZF && !APART) {
     if ((wide = wide_step<D, MT, KT>(p, V))) {
       grid = wide_blocks(p);
       hipLaunchKernelGGL((bdf2_wide_kernel<DIAG, SP, false>), dim3(grid), dim3(kBlock), 0, p->stream, a);
     }
   }
   if (!wide)
-    hipLaunchKernelGGL((bdf2_kernel<D, MT, KT, V, DIAG, SP, false, ZF>), dim3(grid), dim3(SplitShape<D>::kThreads), 0,
+    hipLaunchKernelGGL((bdf2_kernel<D, MT, KT, V, APART, DIAG, SP, false, ZF>), dim3(grid), dim3(SplitShape<D>::kThreads), 0,
                        p->stream, a);
   if (DIAG) hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(kBlock), 0, p->stream, a.part, grid, diag_out);
   return hipGetLastError();
 }
 
 // The spatial form reads FP64 velocity gradients only (an FP32-kappa plan refuses it).
-template <int D, typename MT, typename KT, int V, bool ZF>
+template <int D, typename MT, typename KT, int V, bool APART, bool ZF>
 hipError_t bdf2_go_z(const tfs_plan_s* p, const Bdf2Args<MT, KT>& a, bool diag, double* diag_out) {
   if constexpr (sizeof(KT) == 8) {
     if (a.sp.rate || a.sp.src >= 0)
-      return diag ? bdf2_go_<D, MT, KT, V, true, true, ZF>(p, a, diag_out)
-                  : bdf2_go_<D, MT, KT, V, false, true, ZF>(p, a, diag_out);
+      return diag ? bdf2_go_<D, MT, KT, V, APART, true, true, ZF>(p, a, diag_out)
+                  : bdf2_go_<D, MT, KT, V, APART, false, true, ZF>(p, a, diag_out);
   }
-  return diag ? bdf2_go_<D, MT, KT, V, true, false, ZF>(p, a, diag_out)
-              : bdf2_go_<D, MT, KT, V, false, false, ZF>(p, a, diag_out);
+  return diag ? bdf2_go_<D, MT, KT, V, APART, true, false, ZF>(p, a, diag_out)
+              : bdf2_go_<D, MT, KT, V, APART, false, false, ZF>(p, a, diag_out);
 }
 
-template <int D, typename MT, typename KT, int V>
+template <int D, typename MT, typename KT, int V, bool APART>
 hipError_t bdf2_go(const tfs_plan_s* p, const Bdf2Args<MT, KT>& a, bool diag, double* diag_out) {
-  return p->zform ? bdf2_go_z<D, MT, KT, V, true>(p, a, diag, diag_out)
-                  : bdf2_go_z<D, MT, KT, V, false>(p, a, diag, diag_out);
+  return p->zform ? bdf2_go_z<D, MT, KT, V, APART, true>(p, a, diag, diag_out)
+                  : bdf2_go_z<D, MT, KT, V, APART, false>(p, a, diag, diag_out);
 }
 
 template <int D, typename MT, typename KT>
@@ -962,10 +980,11 @@ hipError_t bdf2_dispatch(const tfs_plan_s* p, int64_t n, const void* ka, const v
   const int V = pick_vec<D, MT, KT>(p, ka, kb, L, tau, 2);
   const bool dg = diag != nullptr;
   if constexpr (sizeof(MT) == 4) {
-    if (V == 4) return bdf2_go<D, MT, KT, 4>(p, a, dg, diag);
+    if (V == 4) return bdf2_go<D, MT, KT, 4, false>(p, a, dg, diag);
   }
-  if (V == 2) return bdf2_go<D, MT, KT, 2>(p, a, dg, diag);
-  return bdf2_go<D, MT, KT, 1>(p, a, dg, diag);
+  if (V == 2) return bdf2_go<D, MT, KT, 2, false>(p, a, dg, diag);
+  if (points_apart<MT>(p)) return bdf2_go<D, MT, KT, kApart<MT>, true>(p, a, dg, diag);
+  return bdf2_go<D, MT, KT, 1, false>(p, a, dg, diag);
 }
 
 template <int D, typename MT, typename KT, int V, bool DIAG, bool SP>
@@ -1004,18 +1023,18 @@ hipError_t start_go(const tfs_plan_s* p, const StartArgs<MT, KT>& a, bool diag, 
 }
 
 // The split step (no local solve, no diagnostics).
-template <int D, typename MT, int V>
+template <int D, typename MT, int V, bool APART>
 hipError_t bdf2_split_go(const tfs_plan_s* p, Bdf2Args<MT, double> a) {
   const SplitGrid sg = split_grid(p, V);
   a.main = sg.main;
   a.wide = sg.wide;
-  if constexpr (D == 2 && sizeof(MT) == 8) {
+  if constexpr (D == 2 && sizeof(MT) == 8 && !APART) {
     if (wide_step<D, MT, double>(p, V)) {
       hipLaunchKernelGGL((bdf2_wide_kernel<false, false, true>), dim3(wide_blocks(p)), dim3(kBlock), 0, p->stream, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((bdf2_kernel<D, MT, double, V, false, false, true>), dim3(sg.grid),
+  hipLaunchKernelGGL((bdf2_kernel<D, MT, double, V, APART, false, false, true>), dim3(sg.grid),
                      dim3(SplitShape<D>::kThreads), 0, p->stream, a);
   return hipGetLastError();
 }
@@ -1050,10 +1069,11 @@ hipError_t bdf2_split_dispatch(const tfs_plan_s* p, int64_t n, const double* ka,
   a.s.tau_scale = p->tau_scale;
   const int V = pick_vec<D, MT, double>(p, ka, kb, L, G, 2);
   if constexpr (sizeof(MT) == 4) {
-    if (V == 4) return bdf2_split_go<D, MT, 4>(p, a);
+    if (V == 4) return bdf2_split_go<D, MT, 4, false>(p, a);
   }
-  if (V == 2) return bdf2_split_go<D, MT, 2>(p, a);
-  return bdf2_split_go<D, MT, 1>(p, a);
+  if (V == 2) return bdf2_split_go<D, MT, 2, false>(p, a);
+  if (points_apart<MT>(p)) return bdf2_split_go<D, MT, kApart<MT>, true>(p, a);
+  return bdf2_split_go<D, MT, 1, false>(p, a);
 }
 
 template <int D, typename MT, typename KT>
@@ -1090,25 +1110,30 @@ hipError_t start_dispatch(const tfs_plan_s* p, const void* ka, const Levels& L, 
   return start_go<D, MT, KT, 1>(p, a, dg, diag);
 }
 
-template <int D, typename MT, typename KT, int V, bool DIAG, bool SP>
+template <int D, typename MT, typename KT, int V, bool APART, bool DIAG, bool SP>
 hipError_t exp_go_(const tfs_plan_s* p, ExpArgs<MT, KT> a, double* diag_out) {
   const SplitGrid sg = split_grid(p, V);
   const int grid = sg.grid;
   a.main = sg.main;
   a.wide = sg.wide;
-  hipLaunchKernelGGL((exp_kernel<D, MT, KT, V, DIAG, SP>), dim3(grid), dim3(SplitShape<D>::kThreads), 0, p->stream, a);
+  hipLaunchKernelGGL((exp_kernel<D, MT, KT, V, APART, DIAG, SP>), dim3(grid), dim3(SplitShape<D>::kThreads), 0, p->stream, a);
   if (DIAG) hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(kBlock), 0, p->stream, a.part, grid, diag_out);
   return hipGetLastError();
+}
+
+template <int D, typename MT, typename KT, int V, bool APART, bool SP>
+hipError_t exp_go_d(const tfs_plan_s* p, const ExpArgs<MT, KT>& a, double* diag) {
+  return diag ? exp_go_<D, MT, KT, V, APART, true, SP>(p, a, diag) : exp_go_<D, MT, KT, V, APART, false, SP>(p, a, diag);
 }
 
 template <int D, typename MT, typename KT, bool SP>
 hipError_t exp_go(const tfs_plan_s* p, const ExpArgs<MT, KT>& a, int V, double* diag) {
   if constexpr (sizeof(MT) == 4) {
-    if (V == 4)
-      return diag ? exp_go_<D, MT, KT, 4, true, SP>(p, a, diag) : exp_go_<D, MT, KT, 4, false, SP>(p, a, diag);
+    if (V == 4) return exp_go_d<D, MT, KT, 4, false, SP>(p, a, diag);
   }
-  if (V == 2) return diag ? exp_go_<D, MT, KT, 2, true, SP>(p, a, diag) : exp_go_<D, MT, KT, 2, false, SP>(p, a, diag);
-  return diag ? exp_go_<D, MT, KT, 1, true, SP>(p, a, diag) : exp_go_<D, MT, KT, 1, false, SP>(p, a, diag);
+  if (V == 2) return exp_go_d<D, MT, KT, 2, false, SP>(p, a, diag);
+  if (points_apart<MT>(p)) return exp_go_d<D, MT, KT, kApart<MT>, true, SP>(p, a, diag);
+  return exp_go_d<D, MT, KT, 1, false, SP>(p, a, diag);
 }
 
 template <int D, typename MT, typename KT>
@@ -1152,12 +1177,12 @@ hipError_t exp_dispatch(const tfs_plan_s* p, int64_t n, const void* ka, const vo
 }
 
 // The split exponential step (no local solve).
-template <int D, typename MT, int V>
+template <int D, typename MT, int V, bool APART>
 hipError_t exp_split_go(const tfs_plan_s* p, ExpArgs<MT, double> a) {
   const SplitGrid sg = split_grid(p, V);
   a.main = sg.main;
   a.wide = sg.wide;
-  hipLaunchKernelGGL((exp_kernel<D, MT, double, V, false, false, true>), dim3(sg.grid), dim3(SplitShape<D>::kThreads),
+  hipLaunchKernelGGL((exp_kernel<D, MT, double, V, APART, false, false, true>), dim3(sg.grid), dim3(SplitShape<D>::kThreads),
                      0, p->stream, a);
   return hipGetLastError();
 }
@@ -1197,10 +1222,11 @@ hipError_t exp_split_dispatch(const tfs_plan_s* p, int64_t n, const double* ka, 
   int V = pick_vec<D, MT, double>(p, ka, a.kb, A, G, sizeof(MT) == 4 ? 4 : 2);
   if (!aligned(H, (size_t)V * 8)) V = 1;
   if constexpr (sizeof(MT) == 4) {
-    if (V == 4) return exp_split_go<D, MT, 4>(p, a);
+    if (V == 4) return exp_split_go<D, MT, 4, false>(p, a);
   }
-  if (V == 2) return exp_split_go<D, MT, 2>(p, a);
-  return exp_split_go<D, MT, 1>(p, a);
+  if (V == 2) return exp_split_go<D, MT, 2, false>(p, a);
+  if (points_apart<MT>(p)) return exp_split_go<D, MT, kApart<MT>, true>(p, a);
+  return exp_split_go<D, MT, 1, false>(p, a);
 }
 
 }  // namespace
