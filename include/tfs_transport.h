@@ -61,8 +61,9 @@ tfs_status tfs_transport_destroy(tfs_transport tr);
  * Transform form, as tfs_ns_batched / tfs_ns_set_batched: 1 when whole fields go through at a time,
  * 0 when planes go through hipFFT one at a time; set_batched(0) forces planes one at a time,
  * set_batched(1) asks for whole fields.  Whole fields go through batched hipFFT plans, tried at
- * creation; 2-D grids of 380000 points or more (160000 with an odd last axis, or an odd stride) with
- * axes of at most 1024 points and no prime factor above 5 use kernels of the library's own.
+ * creation; larger 2-D grids (380000 points or more, down to 250000 for some axes, 160000 with an odd
+ * last axis or an odd stride) with axes of at most 1024 points and no prime factor above 5 use kernels
+ * of the library's own.
  * TFS_EUNSUPPORTED where there is neither: hipFFT refuses the layout, or would get it wrong (an odd
  * stride with an even last axis).  Results agree to rounding.
  */
