@@ -25,7 +25,7 @@
  * (sum_k (X_k^{n+1} - X_k^n) = q X^{n+1} - H), the right-hand side gains T H, and step 3 solves
  * ((1 + q/De) I - q K(kappa~) + q T) X = rhs; there is no start-up step.  Derivatives are spectral
  * (first derivatives with the Nyquist wave number taken as zero); transforms are hipFFT
- * plans made at creation.
+ * plans made at creation, or kernels of the library's own (tfs_transport_batched).
  *
  * Layouts: as tfs.h (grid fields [comp][stride], point index = C-order grid index); the
  * velocity u is [d][stride] FP64.  The object owns its FFT plans and work buffers (about

@@ -3,10 +3,11 @@
 // When kappa(x, t) is a closed-form field (a sum of Fourier terms,
 //   kappa_ij(x, t) = sum_n B_n,ij sin(k_n . x + phi_n + omega_n t)  on [0, 2 pi)^d),
 // no caller interaction is needed between steps: one launch advances every point through
-// K time levels of the exponential-mode scheme (the per-point arithmetic of exp_group,
-// V = 1) with the point's whole state in registers.  The mode level (m c values), X and
-// the previous kappa stay on chip for all K steps; HBM is read once at the start and
-// written once at the end, so the launch is bound by arithmetic, not by memory.
+// K time levels of the exponential-mode scheme (the per-point arithmetic of exp_stream and
+// exp_point) with the point's whole state in registers.  The mode level (m c values) and X
+// stay on chip for all K steps, and the gradient of the step before comes from each term's angle;
+// HBM is read once at the start and written once at the end, so the launch is bound by arithmetic
+// and by the field's LDS reads, not by memory.
 //
 // Per point and step: kappa at t_n evaluated from the field (FP64 sine per term), the
 // half-step gradient kappa~ = 3/2 kappa^n - 1/2 kappa^{n-1} (kappa^0 at n = 0), the mode

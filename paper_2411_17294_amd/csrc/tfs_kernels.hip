@@ -1,7 +1,9 @@
 // HIP kernels (gfx950) of the time-fractional extra-stress update.
 //
-// One lane owns V consecutive points of the structure-of-arrays fields and runs the
-// whole step for them in registers:
+// The BDF2 and exponential steps run in blocks of six waves, one per tensor component: a wave streams
+// its component's modes for a few points a lane, and the point's sums meet in LDS, where one lane per
+// point solves the local system.  (The start-up, and BDF2 on whole 2-D FP64 grids, keep all components
+// of a point in one lane.)
 //   * BDF2 step (Sec. 4.1, eqs. BDF_Phi_k_n+1 and FP_discrete, pointwise in tensor
 //     variables with the mode representation Y_k = X_k - c_k X):
 //       P        = 2 X^n - X^{n-1}/2
@@ -10,16 +12,15 @@
 //       [(b0 + eta/De) I - eta (kappa~ . + . kappa~^T)] X^{n+1} = P - A(G) + zeta^{n+1} S
 //       tau^{n+1} = (gamma/dt) (eta X^{n+1} - G)
 //     The modes are streamed once: two levels read, one level written into the slot of
-//     the older level.  The c x c local system (c = 3 or 6) is solved per lane by
+//     the older level.  The c x c local system (c = 3 or 6) is solved in a lane's registers by
 //     Gaussian elimination with partial pivoting.
 //   * SDIRK2 start-up (first step from rest of the modes): two stage solves with the
 //     same local matrix; the level-0 and level-1 modes are written.
 //   * Exponential-mode step (an extension, not the paper's scheme): every mode solved
 //     exactly for X linear on the step, one mode level updated in place, and the state
 //     integrated as X^{n+1} - X^n = A(sum_k (X_k^{n+1} - X_k^n)) + zeta S.
-// The mode loop is a pure stream (no MFMA: about one flop per byte); global loads of
-// the next mode are issued before the stores of the current one, so several KB per
-// wave are in flight.
+// The mode loop is a pure stream (no MFMA: about one flop per byte); the loads of the next two to
+// eight modes are in flight while one is worked on (stream_modes).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -767,7 +768,8 @@ __device__ __forceinline__ void exp_point(const ExpArgs<MT, KT>& a, int64_t pw, 
 }
 
 // Blocks, waves and lanes as in bdf2_kernel (3-D, m = 32, FP32 modes, 128^3: 654 us, 0.73 of
-// 8 TB/s, was 660; 4096 points, 2-D, FP64: 8.7 us, was 18.3).
+// 8 TB/s, was 660; 4096 points, 2-D, FP64: 8.7 us, was 18.3).  The first step only writes modes
+// (884736 points, FP32 modes: 149 us, bound by its stores).
 // SPLIT: the step without its local solve, for a caller that solves a spatially coupled
 // system: X^{n+1} receives each point's right-hand side R, tau the compensated G and Hout the
 // H of the local system (the modes are written as usual: they do not depend on X^{n+1}).
