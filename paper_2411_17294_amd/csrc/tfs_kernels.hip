@@ -114,19 +114,20 @@ struct SplitShape {
 struct SplitWave { int lane, s, group; };
 
 // The rounds of a component-split launch.  The first `wide` blocks take `main` blocks of points at
-// V points a lane (all of them whole) in turn; the others take the points after them at one point
-// a lane, 64 kGroups a round, beside the first ones: what would be a nearly empty last round of
-// wide blocks runs along with the full ones, and the ragged end of the field needs no launch of its
-// own.  body(width, wave, first point, points left, half): half alternates, so that one barrier a
-// round (between the streams and the solves) is enough for LDS that is kept twice.
+// V points a lane (all of them whole) in turn, or, `chunked`, consecutive ones each; the others take
+// the points after them at one point a lane, 64 kGroups a round, beside the first ones: what would be a
+// nearly empty last round of wide blocks runs along with the full ones, and the ragged end of the field
+// needs no launch of its own.  body(width, wave, first point, points left, half): half alternates, so
+// that one barrier a round (between the streams and the solves) is enough for LDS that is kept twice.
 template <int D, int V, typename F>
-__device__ __forceinline__ void split_rounds(int64_t npoints, int64_t main, int wide, F&& body) {
+__device__ __forceinline__ void split_rounds(int64_t npoints, int64_t main, int wide, int chunked, F&& body) {
   constexpr int C = Sym<D>::C, N1 = 64 * SplitShape<D>::kGroups;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const SplitWave sw{(int)threadIdx.x % 64, wid % C, wid / C};
   int half = 0;
   if ((int)blockIdx.x < wide) {
-    for (int64_t g = blockIdx.x; g < main; g += wide, half ^= 1)
+    const int64_t step = chunked ? 1 : wide, end = chunked ? main * (blockIdx.x + 1) / wide : main;
+    for (int64_t g = chunked ? main * blockIdx.x / wide : blockIdx.x; g < end; g += step, half ^= 1)
       body(std::integral_constant<int, V>{}, sw, g * (N1 * V), npoints - g * (N1 * V), half);
   } else {
     const int64_t step = (int64_t)(gridDim.x - wide) * N1;
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(SplitShape<D>::kThreads) void bdf2_kernel(const Bdf
   constexpr int C = Sym<D>::C;
   __shared__ double sh[2][2 * C * SplitShape<D>::kGroups * 64 * V];
   DiagAcc acc;
-  split_rounds<D, V>(a.npoints, a.main, a.wide, [&](auto width, const SplitWave& sw, int64_t pw, int64_t left, int half) {
+  split_rounds<D, V>(a.npoints, a.main, a.wide, 0, [&](auto width, const SplitWave& sw, int64_t pw, int64_t left, int half) {
     constexpr int W = decltype(width)::value, NP = SplitShape<D>::kGroups * 64 * W, T = SplitShape<D>::kThreads;
     constexpr int Q = (NP + T - 1) / T, A = sizeof(MT) * W >= 16 ? 2 : 4;
     KappaAt<D, KT> kap[Q];
@@ -662,7 +663,8 @@ struct ExpArgs {
   const double* coef;   // [kNumCoef][m], ExpRow order
   double* part;         // block partials or null
   int64_t npoints, main;   // main, wide: blocks of points at V points a lane, and the blocks that
-  int wide;                // take them (split_rounds)
+  int wide;                // take them, consecutive ones a block where chunked (split_rounds)
+  int chunked;
   int64_t stride, tile;
   int m;
   ExpScalars s;
@@ -778,7 +780,7 @@ __global__ __launch_bounds__(SplitShape<D>::kThreads) void exp_kernel(const ExpA
   constexpr int C = Sym<D>::C;
   __shared__ double sh[2][3 * C * SplitShape<D>::kGroups * 64 * V];
   DiagAcc acc;
-  split_rounds<D, V>(a.npoints, a.main, a.wide, [&](auto width, const SplitWave& sw, int64_t pw, int64_t left, int half) {
+  split_rounds<D, V>(a.npoints, a.main, a.wide, a.chunked, [&](auto width, const SplitWave& sw, int64_t pw, int64_t left, int half) {
     constexpr int W = decltype(width)::value, NP = SplitShape<D>::kGroups * 64 * W, T = SplitShape<D>::kThreads;
     constexpr int Q = (NP + T - 1) / T, A = sizeof(MT) * W >= 16 ? 4 : 8;
     KappaAt<D, KT> kap[Q];
@@ -875,6 +877,11 @@ SplitGrid split_grid(const tfs_plan_s* p, int V) {
   const int64_t wide = std::min(cap, main);
   return {(int)(wide + std::min(cap, narrow)), (int)wide, main};
 }
+
+// Whether an exponential step's blocks take consecutive blocks of points: large 3-D FP64 grids (m = 40,
+// 2^24 points 11883 us in turn, 10903 so; 2^22 2898 and 2860; but 884736 points, m = 32, 451 and 467).
+template <int D, typename MT>
+int chunked_rounds(const tfs_plan_s* p) { return D == 3 && sizeof(MT) == 8 && p->npoints >= (1 << 21); }
 
 // The mean share of the CUs that is busy when blocks of `per` points go round by round.
 double fill(const tfs_plan_s* p, int64_t per) {
@@ -1118,6 +1125,7 @@ hipError_t exp_go_(const tfs_plan_s* p, ExpArgs<MT, KT> a, double* diag_out) {
   const int grid = sg.grid;
   a.main = sg.main;
   a.wide = sg.wide;
+  a.chunked = chunked_rounds<D, MT>(p);
   hipLaunchKernelGGL((exp_kernel<D, MT, KT, V, APART, DIAG, SP>), dim3(grid), dim3(SplitShape<D>::kThreads), 0, p->stream, a);
   if (DIAG) hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(kBlock), 0, p->stream, a.part, grid, diag_out);
   return hipGetLastError();
@@ -1184,6 +1192,7 @@ hipError_t exp_split_go(const tfs_plan_s* p, ExpArgs<MT, double> a) {
   const SplitGrid sg = split_grid(p, V);
   a.main = sg.main;
   a.wide = sg.wide;
+  a.chunked = chunked_rounds<D, MT>(p);
   hipLaunchKernelGGL((exp_kernel<D, MT, double, V, APART, false, false, true>), dim3(sg.grid), dim3(SplitShape<D>::kThreads),
                      0, p->stream, a);
   return hipGetLastError();
